@@ -48,11 +48,11 @@ template <> struct CellsFor<16, 8> { using L = Cells<16, 8, 2, 1>; };
 template <int TW, int TH> struct FwdCellsFor { using L = typename CellsFor<TW, TH>::L; };
 template <> struct FwdCellsFor<16, 16> { using L = Cells<16, 16, 2, 1>; };
 
-// Finer cells for launches of few tiles (one lane still owns one cell): 1 x 1
-// where the backward's are 2 x 2 or 2 x 1 (16-wide tiles), 2 x 1 where they
-// are 2 x 2 (32-wide ones).  Such a launch does not fill the chip's wave
-// slots, so it takes as long as its longest lists, and every wave of a tile
-// that shares the work shortens those.
+// The forward's finer cells for launches of few tiles (one lane still owns
+// one cell): 1 x 1 where the backward's are 2 x 2 or 2 x 1 (16-wide tiles), 2
+// x 1 where they are 2 x 2 (32-wide ones).  Such a launch does not fill the
+// chip's wave slots, so it takes as long as its longest lists, and every wave
+// of a tile that shares the work shortens those.
 template <int TW, int TH> struct FineCellsFor { using L = Cells<TW, TH, 2, 1>; };
 template <> struct FineCellsFor<8, 8> { using L = typename CellsFor<8, 8>::L; };   // already 1 x 1
 template <> struct FineCellsFor<16, 8> { using L = Cells<16, 8, 1, 1>; };
@@ -75,7 +75,7 @@ template <> struct FineCellsFor<16, 16> { using L = Cells<16, 16, 1, 1>; };
 // turned into cells (a superset: covering a few more only costs
 // evaluations that the blend then skips).  x0: the tile's first pixel
 // column, y0: the wave's first pixel row (image coordinates).
-template <class L>
+template <class L, int ROWS = L::ROWS_W>
 __device__ __forceinline__ uint64_t cell_mask(const Staged& g, int x0, int y0) {
     const float ca = g.coef.x, cb = g.coef.y, cc = g.coef.z;
     const float thm = g.col.w - (2e-3f + 2e-4f * fabsf(g.col.w));
@@ -89,7 +89,7 @@ __device__ __forceinline__ uint64_t cell_mask(const Staged& g, int x0, int y0) {
     const float xs_lo = xs - 1e-3f, xs_hi = xs + 1e-3f;
     uint32_t lo = 0u, hi = 0u;
 #pragma unroll
-    for (int r = 0; r < L::ROWS_W; ++r) {
+    for (int r = 0; r < ROWS; ++r) {
         float cl = __builtin_inff(), ch = -__builtin_inff();   // merged chord of the cell row
 #pragma unroll
         for (int q = 0; q < L::CH; ++q) {

@@ -30,9 +30,15 @@
 // atomics, to the entry's (Gaussian, tile) pair slot in emission order; a
 // gather then adds each Gaussian's pair slots, so the per-Gaussian sum has
 // a fixed order.  A chunk ends early when its entries' slots would exceed
-// the LDS capacity (Gaussians that reach many cells).  With several waves a
-// tile, each wave adds its own slots of an entry first and the entry's
-// thread then the waves' sums, in wave order.
+// the LDS capacity (Gaussians that reach many cells).
+//
+// Small launches give each cell to several lanes (Team): every lane takes
+// some of the cell's pixels and its own share of the walk, and the pixels'
+// terms are then summed in the order of the one lane, which DPP moves bring
+// them in.  So the order of no sum depends on the size of the launch, and a
+// view's gradients are the same bits either way: the projection's chain rule
+// magnifies the rounding of these sums (a large Gaussian's scale gradient
+// moved by 1e-3 where a cell's pixels were summed through slots of their own).
 #include "blend_cells.h"
 #include "kernels.h"
 #include "tile_order.h"
@@ -73,38 +79,85 @@ struct BwdArgs {
     const uint32_t* torder_n;   // ... and exits when b >= *torder_n
 };
 
-// Launches whose tiles give at most kFineBwdWaves waves (about seven a CU in
-// the usual layout) take the fine cells, with slots for the more numerous
-// items.  Measured, usual -> fine: 200k Gaussians at 800 x 800 (2500 tiles of
-// 16 x 16) 191 -> 143 us, 600 x 500 292 -> 198 us, 1M at 700 x 700 542 -> 409
-// us, 20k at 400 x 400 47 -> 35 us; the other shapes at 2500 waves 190 -> 155
-// (32 x 8), 273 -> 230 (32 x 16), 389 -> 343 us (32 x 32).  Above, the
-// additional items cost more than they save: 400k at 1200 x 900 (4275 tiles)
-// 223 -> 305 us, 1M at 1920 x 1080 218 -> 516 us.  The fine cells' masks are
-// recomputed (each wave's rows are fewer), the ones the forward kept are not
-// read.
-constexpr int64_t kFineBwdWaves = 2560;
-constexpr int kFineCap = 2048;
+// Launches whose tiles give at most kTeamMaxWaves waves of one lane a cell
+// (ten a CU) take kTeamLanes lanes a cell (two where a cell has two pixels),
+// with more slots.  Such a launch takes as long as its longest lists, and the
+// walk is shorter: a lane evaluates one pixel instead of four, and a wave
+// waits for the longest of 16 cells' lists instead of 64.  Measured, one lane
+// -> team: 2000 Gaussians at 128 x 128 (64 tiles of 16 x 16) 91 -> 56 us, 20k
+// at 400 x 400 49 -> 40, 200k at 800 x 800 (2500 tiles) 194 -> 158, at 600 x
+// 500 298 -> 237; 200k at 800 x 800 in tiles of 32 x 8 191 -> 160 (2500
+// waves), of 32 x 16 271 -> 224, of 32 x 32 375 -> 325; 200k at 672 x 480 in
+// tiles of 16 x 8 (2520 waves) 128 -> 127.  The team issues more instructions
+// in all, so it loses once the chip is full, from 2900 waves on with few
+// Gaussians and 4900 with many: 2478 waves 41 -> 40 (20k Gaussians), 95 -> 79
+// (100k), 254 -> 207 (400k) and 430 -> 350 (1M); 3381: 47 -> 49, 93 -> 91,
+// 215 -> 174 and 360 -> 319; 4368: 53 -> 59, 91 -> 102, 191 -> 176 and 307 ->
+// 330; 5185: 58 -> 68, 93 -> 112, 177 -> 186 and 294 -> 339.  The line is the
+// largest size at which it gained everywhere.  512 slots: 69 us for the box;
+// 2048: as 1024 there, 208 at 800 x 800.
+constexpr int64_t kTeamMaxWaves = 2560;
+constexpr int kTeamLanes = 4;
+constexpr int kTeamCap = 1024;
 
-template <class L, int CAP>
+// LPC lanes of a wave share each cell (consecutive lanes, an equal part of
+// the cell's pixels each, in pixel order).
+template <class L, int LPC>
+struct Team {
+    static constexpr int THREADS = L::NCELL * LPC;
+    static constexpr int WAVES = THREADS / kWave;
+    static constexpr int CELLS_W = kWave / LPC;         // cells per wave
+    static constexpr int ROWS_W = CELLS_W / L::CPR;     // cell rows per wave
+    static constexpr int PPL = L::NP / LPC;             // pixels per lane
+    static_assert(LPC == 1 || LPC == 2 || LPC == 4, "lanes of a cell lie in a quad");
+    static_assert(L::NP % LPC == 0 && CELLS_W % L::CPR == 0, "cell layout");
+};
+
+// Pixel values own[] of a cell's lanes -> the values of all its pixels, in
+// every one of them.
+template <int LPC, int PPL>
+__device__ __forceinline__ void share(const float (&own)[PPL], float (&all)[PPL * LPC]) {
+#pragma unroll
+    for (int k = 0; k < PPL; ++k) {
+        const int v = __float_as_int(own[k]);
+        if constexpr (LPC == 1) {
+            all[k] = own[k];
+        } else if constexpr (LPC == 2) {
+            all[k] = __int_as_float(__builtin_amdgcn_mov_dpp(v, 0xA0, 0xF, 0xF, true));         // quad_perm 0 0 2 2
+            all[PPL + k] = __int_as_float(__builtin_amdgcn_mov_dpp(v, 0xF5, 0xF, 0xF, true));   // quad_perm 1 1 3 3
+        } else {
+            all[k] = __int_as_float(__builtin_amdgcn_mov_dpp(v, 0x00, 0xF, 0xF, true));
+            all[PPL + k] = __int_as_float(__builtin_amdgcn_mov_dpp(v, 0x55, 0xF, 0xF, true));
+            all[2 * PPL + k] = __int_as_float(__builtin_amdgcn_mov_dpp(v, 0xAA, 0xF, 0xF, true));
+            all[3 * PPL + k] = __int_as_float(__builtin_amdgcn_mov_dpp(v, 0xFF, 0xF, 0xF, true));
+        }
+    }
+}
+
+template <class L, int LPC, int CAP>
 struct BwdShared {
+    static constexpr int WAVES = Team<L, LPC>::WAVES;
     // one entry can reach every cell of the workgroup: its slots must fit,
     // or a chunk could not take even its top candidate
     static_assert(CAP >= L::NCELL, "slot capacity below the cells of a tile");
     Staged s[kChunk];
     uint32_t gid[kChunk];
-    uint64_t mask[L::WAVES][kChunk];   // per wave: the cells that walk each entry
-    uint32_t base[L::WAVES][kChunk];   // items per (wave, entry), then their first slot
-    float item[9][CAP];                // the nine sums of each (cell, entry)
+    uint64_t mask[WAVES][kChunk];   // per wave: the cells that walk each entry
+    uint32_t base[WAVES][kChunk];   // items per (wave, entry), then their first slot
+    uint32_t total[kChunk];         // items per entry
+    float item[9][CAP];             // the nine sums of each (cell, entry)
+    float sum[WAVES > 1 ? 9 : 1][kChunk];   // ... and of each entry
     uint32_t max_last;
-    int kmin;                          // the chunk: candidates kmin .. ncand - 1
+    int kmin;                       // the chunk: candidates kmin .. ncand - 1
 };
 
 // STORED = true reads each entry's (alpha, T) from the state the storing
 // forward wrote (alpha negated when capped) instead of recomputing them.
-template <class L, bool STORED, int CAP>
-__device__ __forceinline__ void bwd_tile(const BwdArgs& a, uint32_t tile, BwdShared<L, CAP>& sh) {
-    constexpr int NP = L::NP;
+template <class L, int LPC, bool STORED, int CAP>
+__device__ __forceinline__ void bwd_tile(const BwdArgs& a, uint32_t tile, BwdShared<L, LPC, CAP>& sh) {
+    using Tm = Team<L, LPC>;
+    constexpr int NP = L::NP, PPL = Tm::PPL, WAVES = Tm::WAVES;
+    static_assert(!STORED || LPC == 1, "the stored form has one lane a cell");
     if (*a.status != 0) return;
 
     const View V = view_at(a.views, find_view(a.views, tile));
@@ -112,9 +165,11 @@ __device__ __forceinline__ void bwd_tile(const BwdArgs& a, uint32_t tile, BwdSha
     const int local = (int)(tile - V.tile_base);
     const int tx = local % V.ntx, ty = local / V.ntx;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
-    const int cx = tid % L::CPR, cy = tid / L::CPR;
+    const int cell = tid / LPC, wcell = lane / LPC;   // the lane's cell in the tile, in the wave
+    const int sub = tid % LPC;                        // its part of the cell: pixels sub PPL ..
+    const int cx = cell % L::CPR, cy = cell / L::CPR;
     const int x0 = tx * L::TW, y0 = ty * L::TH;
-    const int wy0 = y0 + wv * L::PXROWS_W;
+    const int wy0 = y0 + wv * (Tm::ROWS_W * L::CH);
     const int64_t npix = (int64_t)W * H;
     const float* final_T = a.final_T + V.pix_base;
     const uint32_t* n_contrib = a.n_contrib + V.pix_base;
@@ -129,28 +184,37 @@ __device__ __forceinline__ void bwd_tile(const BwdArgs& a, uint32_t tile, BwdSha
 #pragma unroll
     for (int j = 0; j < L::CH; ++j) fyp[j] = (float)(py0 + j) + 0.5f;
 
-    uint32_t my_last[NP];
-    float T[NP], g0[NP], g1[NP], g2[NP], ga[NP];
+    uint32_t my_last[PPL];
+    float T[PPL], o0[PPL], o1[PPL], o2[PPL], ga[PPL];   // the lane's pixels
+    float g0[NP], g1[NP], g2[NP];                       // dL/dpixel of the whole cell
     uint32_t cell_last = 0;
 #pragma unroll
-    for (int p = 0; p < NP; ++p) {
+    for (int k = 0; k < PPL; ++k) {
+        const int p = sub * PPL + k;
         const int x = px0 + p % L::CW, y = py0 + p / L::CW;
-        my_last[p] = 0u;
-        T[p] = 1.0f;
-        g0[p] = g1[p] = g2[p] = 0.0f;
+        my_last[k] = 0u;
+        T[k] = 1.0f;
+        o0[k] = o1[k] = o2[k] = 0.0f;
         if (x < W && y < H) {
             const int64_t off = (int64_t)y * W + x;
-            my_last[p] = n_contrib[off];
-            T[p] = final_T[off];
-            g0[p] = dimg[off];
-            g1[p] = dimg[npix + off];
-            g2[p] = dimg[2 * npix + off];
+            my_last[k] = n_contrib[off];
+            T[k] = final_T[off];
+            o0[k] = dimg[off];
+            o1[k] = dimg[npix + off];
+            o2[k] = dimg[2 * npix + off];
         }
         // g . S, S the colour behind the current entry: the background's
         // share T_final bg, then the blended rgb_j w_j as they are passed
-        ga[p] = g0[p] * (T[p] * bg0) + g1[p] * (T[p] * bg1) + g2[p] * (T[p] * bg2);
-        cell_last = max(cell_last, my_last[p]);
+        ga[k] = o0[k] * (T[k] * bg0) + o1[k] * (T[k] * bg1) + o2[k] * (T[k] * bg2);
+        cell_last = max(cell_last, my_last[k]);
     }
+    share<LPC, PPL>(o0, g0);
+    share<LPC, PPL>(o1, g1);
+    share<LPC, PPL>(o2, g2);
+    if (LPC >= 2) cell_last = max(cell_last, xor_lane(cell_last, 1));
+    if (LPC >= 4) cell_last = max(cell_last, xor_lane(cell_last, 2));
+    // the last contributor of the wave's cell number `lane`
+    const uint32_t word_last = LPC == 1 ? cell_last : (uint32_t)__shfl((int)cell_last, lane * LPC % kWave, kWave);
 
     __syncthreads();   // the previous tile of a persistent workgroup is done with the shared state
     if (tid == 0) sh.max_last = 0u;
@@ -184,7 +248,7 @@ __device__ __forceinline__ void bwd_tile(const BwdArgs& a, uint32_t tile, BwdSha
         const int lo0 = hi > kChunk ? hi - kChunk : 0;
         const int last = hi - lo0 - 1;
         vk = a.vals[rg.x + (uint32_t)(lo0 + min(tid, last))];
-        if (a.masks) mk = a.masks[(int64_t)(rg.x + (uint32_t)(lo0 + min(lane, last))) * L::WAVES + wv];
+        if (a.masks) mk = a.masks[(int64_t)(rg.x + (uint32_t)(lo0 + min(lane, last))) * L::WAVES + wv / LPC];
         rk = a.rec[vk];
     }
     while (hi > 0) {
@@ -199,7 +263,8 @@ __device__ __forceinline__ void bwd_tile(const BwdArgs& a, uint32_t tile, BwdSha
 
         // entry-major cell masks of this wave, transposed into the lane's
         // walk word, cut at the cell's last contributor, and back
-        const uint64_t m = lane < ncand ? (a.masks ? mk : cell_mask<L>(sh.s[lane], x0, wy0)) : 0ull;
+        if (LPC > 1) mk = mk >> (Tm::CELLS_W * (wv % LPC)) & ((1ull << (Tm::CELLS_W % kWave)) - 1ull);
+        const uint64_t m = lane < ncand ? (a.masks ? mk : cell_mask<L, Tm::ROWS_W>(sh.s[lane], x0, wy0)) : 0ull;
         if (ds >= 0) {   // the previous chunk's pair slot
             a.pg8[2 * ds] = d0;
             a.pg8[2 * ds + 1] = d1;
@@ -208,10 +273,13 @@ __device__ __forceinline__ void bwd_tile(const BwdArgs& a, uint32_t tile, BwdSha
         }
         uint64_t walk = transpose64(m, lane);
         {
-            const int lim = (int)cell_last - lo0;   // entries lo0 + k with k < lim
+            const int lim = (int)word_last - lo0;   // entries lo0 + k with k < lim
             walk = lim <= 0 ? 0ull : (lim >= kWave ? walk : (walk & ((1ull << lim) - 1ull)));
         }
         const uint64_t mw = transpose64(walk, lane);
+        if (LPC > 1)   // the lane's cell's word
+            walk = ((uint64_t)(uint32_t)__shfl((int)(uint32_t)(walk >> 32), wcell, kWave) << 32) |
+                   (uint32_t)__shfl((int)(uint32_t)walk, wcell, kWave);
         sh.mask[wv][lane] = mw;
         sh.base[wv][lane] = (uint32_t)__popcll(mw);
         __syncthreads();
@@ -221,7 +289,7 @@ __device__ __forceinline__ void bwd_tile(const BwdArgs& a, uint32_t tile, BwdSha
         if (wv == 0) {
             uint32_t tot = 0;
 #pragma unroll
-            for (int w = 0; w < L::WAVES; ++w) tot += sh.base[w][lane];
+            for (int w = 0; w < WAVES; ++w) tot += sh.base[w][lane];
             // inclusive suffix sum over the candidates above (k >= lane)
             uint32_t suf = tot;
 #pragma unroll
@@ -234,11 +302,12 @@ __device__ __forceinline__ void bwd_tile(const BwdArgs& a, uint32_t tile, BwdSha
             if (lane == 0) sh.kmin = inm ? low_bit(inm) : ncand;
             uint32_t b = suf - tot;   // slots of the entries above
 #pragma unroll
-            for (int w = 0; w < L::WAVES; ++w) {
+            for (int w = 0; w < WAVES; ++w) {
                 const uint32_t c = sh.base[w][lane];
                 sh.base[w][lane] = b;
                 b += c;
             }
+            sh.total[lane] = tot;
         }
         __syncthreads();
         const int kmin = sh.kmin;
@@ -250,7 +319,7 @@ __device__ __forceinline__ void bwd_tile(const BwdArgs& a, uint32_t tile, BwdSha
             const int nlo = nhi > kChunk ? nhi - kChunk : 0;
             const int nlast = max(nhi - nlo - 1, 0);
             vk = a.vals[rg.x + (uint32_t)(nlo + min(tid, nlast))];
-            if (a.masks) mk = a.masks[(int64_t)(rg.x + (uint32_t)(nlo + min(lane, nlast))) * L::WAVES + wv];
+            if (a.masks) mk = a.masks[(int64_t)(rg.x + (uint32_t)(nlo + min(lane, nlast))) * L::WAVES + wv / LPC];
         }
 
         // walk: entries kmin .. ncand - 1 of the lane's word, from the back.
@@ -258,7 +327,7 @@ __device__ __forceinline__ void bwd_tile(const BwdArgs& a, uint32_t tile, BwdSha
         // while the current entry is computed (a lane whose word is empty
         // reads entry kmin, which exists, and writes nothing).
         uint64_t wk = kmin >= kWave ? 0ull : (walk & ~((1ull << kmin) - 1ull));
-        const uint64_t below = (1ull << lane) - 1ull;
+        const uint64_t below = (1ull << wcell) - 1ull;
         // one walked entry: its nine sums for the lane's cell, written to
         // the lane's slot
         auto entry = [&](const bool has, const int kk, const Staged& g, const uint32_t sbase, const uint64_t smask) {
@@ -267,20 +336,33 @@ __device__ __forceinline__ void bwd_tile(const BwdArgs& a, uint32_t tile, BwdSha
             const uint32_t pos = has ? (uint32_t)(lo0 + kk) : 0xFFFFFFFFu;
             // the forward's exponent: dx (ca dx + cb dy) + cc dy^2, the dy
             // terms once per pixel row
-            float dxs[L::CW], dys[L::CH], rb[L::CH], rc[L::CH];
+            // (OH: the rows of the lane's own pixels)
+            constexpr int OH = LPC == 1 ? L::CH : 1;
+            float dxs[L::CW], dys[L::CH], oy[OH], rb[OH], rc[OH];
 #pragma unroll
             for (int i = 0; i < L::CW; ++i) dxs[i] = (fxp[i] - g.geo.x) - g.geo.y;
 #pragma unroll
-            for (int j = 0; j < L::CH; ++j) {
-                dys[j] = (fyp[j] - g.geo.z) - g.geo.w;
-                rb[j] = g.coef.y * dys[j];
-                rc[j] = (g.coef.z * dys[j]) * dys[j];
+            for (int j = 0; j < L::CH; ++j) dys[j] = (fyp[j] - g.geo.z) - g.geo.w;
+            const float ox = PPL == 1 && sub % L::CW ? dxs[L::CW - 1] : dxs[0];
+#pragma unroll
+            for (int j = 0; j < OH; ++j) {
+                oy[j] = LPC == 1 ? dys[j] : sub * PPL / L::CW ? dys[L::CH - 1] : dys[0];
+                rb[j] = g.coef.y * oy[j];
+                rc[j] = (g.coef.z * oy[j]) * oy[j];
             }
             // the cell's sums: dL/do, dL/drgb, and dL/dpower per pixel
             float s5 = 0.f, s6 = 0.f, s7 = 0.f, s8 = 0.f, dpow[NP];
+            float ow[PPL], oda[PPL], oG[PPL], opow[PPL];
+            auto add = [&](int p, float w, float da, float G) {
+                s6 = __builtin_fmaf(g0[p], w, s6);
+                s7 = __builtin_fmaf(g1[p], w, s7);
+                s8 = __builtin_fmaf(g2[p], w, s8);
+                s5 = __builtin_fmaf(da, G, s5);
+            };
 #pragma unroll
-            for (int p = 0; p < NP; ++p) {
+            for (int p = 0; p < PPL; ++p) {
                 const int i = p % L::CW, j = p / L::CW;
+                const float dx = PPL == 1 ? ox : dxs[i];
                 float alpha, G, Ts;
                 bool capped, above;
                 const bool listed = pos < my_last[p];
@@ -295,7 +377,7 @@ __device__ __forceinline__ void bwd_tile(const BwdArgs& a, uint32_t tile, BwdSha
                 } else {
                     // the forward's decision: alpha (capped at 0.99) counts
                     // when the exponent is not positive and alpha >= 1/255
-                    const float pw = __builtin_fmaf(dxs[i], __builtin_fmaf(g.coef.x, dxs[i], rb[j]), rc[j]);
+                    const float pw = __builtin_fmaf(dx, __builtin_fmaf(g.coef.x, dx, rb[j]), rc[j]);
                     G = __builtin_amdgcn_exp2f(pw);
                     const float araw = g.coef.w * G;
                     capped = araw > kAlphaMax;
@@ -311,18 +393,31 @@ __device__ __forceinline__ void bwd_tile(const BwdArgs& a, uint32_t tile, BwdSha
                 const float iom = __builtin_amdgcn_rcpf(1.0f - al);
                 const float Ti = STORED ? (contrib ? Ts : T[p]) : T[p] * iom;
                 const float w = al * Ti;
-                const float grgb = __builtin_fmaf(g2[p], g.col.z, __builtin_fmaf(g1[p], g.col.y, g0[p] * g.col.x));
+                const float grgb = __builtin_fmaf(o2[p], g.col.z, __builtin_fmaf(o1[p], g.col.y, o0[p] * g.col.x));
                 // dL/dalpha = g . (rgb T_i - S_i / (1 - alpha)), S_i = suffix colour + T_final bg;
                 // no gradient through a capped alpha
                 const float da0 = __builtin_fmaf(grgb, Ti, -(ga[p] * iom));
                 const float da = (contrib && !capped) ? da0 : 0.0f;
                 ga[p] = __builtin_fmaf(grgb, w, ga[p]);
                 T[p] = Ti;
-                s6 = __builtin_fmaf(g0[p], w, s6);
-                s7 = __builtin_fmaf(g1[p], w, s7);
-                s8 = __builtin_fmaf(g2[p], w, s8);
-                s5 = __builtin_fmaf(da, G, s5);
-                dpow[p] = da * al;
+                if constexpr (LPC == 1) {
+                    add(p, w, da, G);
+                    dpow[p] = da * al;
+                } else {
+                    ow[p] = w;
+                    oda[p] = da;
+                    oG[p] = G;
+                    opow[p] = da * al;
+                }
+            }
+            if constexpr (LPC > 1) {   // the cell's pixels in the same order, in each of its lanes
+                float cw[NP], cda[NP], cG[NP];
+                share<LPC, PPL>(ow, cw);
+                share<LPC, PPL>(oda, cda);
+                share<LPC, PPL>(oG, cG);
+                share<LPC, PPL>(opow, dpow);
+#pragma unroll
+                for (int p = 0; p < NP; ++p) add(p, cw[p], cda[p], cG[p]);
             }
             // moments of dL/dpower over the pixel offsets (the centre and
             // conic gradients are linear in them, formed at the flush):
@@ -361,8 +456,9 @@ __device__ __forceinline__ void bwd_tile(const BwdArgs& a, uint32_t tile, BwdSha
                 s1 += u;
                 s4 = __builtin_fmaf(u, dys[j], s4);
             }
-            if (has) {
-                const uint32_t slot = sbase + (uint32_t)__popcll(smask & below);
+            if (has && sub == 0) {
+                const uint32_t slot =
+                    sbase + (uint32_t)(LPC == 1 ? __popcll(smask & below) : __popc((uint32_t)smask & (uint32_t)below));
                 sh.item[0][slot] = s0;
                 sh.item[1][slot] = s1;
                 sh.item[2][slot] = s2;
@@ -409,29 +505,39 @@ __device__ __forceinline__ void bwd_tile(const BwdArgs& a, uint32_t tile, BwdSha
         // du = sum dpow (A dx + B dy), dv = sum dpow (B dx + C dy),
         // dA = -sum dpow dx^2 / 2, dB = -sum dpow dx dy, dC = -sum dpow dy^2 / 2,
         // where A = -2 ca / log2e, B = -cb / log2e, C = -2 cc / log2e.
-        // One thread per entry adds the entry's slots in order and writes
+        // One thread per entry adds the entry's slots in order (with several
+        // waves, wave w of them the sums w, w + WAVES, ...) and one writes
         // its pair slot (no atomics).
         float sum[9];
+        if constexpr (WAVES == 1) {
 #pragma unroll
-        for (int c = 0; c < 9; ++c) sum[c] = 0.0f;
-        if (lane >= kmin && lane < ncand) {
-            const uint32_t b = sh.base[wv][lane], n = (uint32_t)__popcll(sh.mask[wv][lane]);
-            for (uint32_t e = b; e < b + n; ++e) {
+            for (int c = 0; c < 9; ++c) sum[c] = 0.0f;
+            if (tid >= kmin && tid < ncand) {
+                const uint32_t b = sh.base[0][tid], n = sh.total[tid];
+                for (uint32_t e = b; e < b + n; ++e) {
 #pragma unroll
-                for (int c = 0; c < 9; ++c) sum[c] += sh.item[c][e];
+                    for (int c = 0; c < 9; ++c) sum[c] += sh.item[c][e];
+                }
             }
-        }
-        if (L::WAVES > 1) {
-            __syncthreads();   // every slot is read: the waves' sums take their place
+        } else {
+            constexpr int PER = (9 + WAVES - 1) / WAVES;
+            const int w0 = __builtin_amdgcn_readfirstlane(wv);
+            if (w0 < 9 && lane >= kmin && lane < ncand) {
+                const uint32_t b = sh.base[0][lane], n = sh.total[lane];
+                float part[PER];
 #pragma unroll
-            for (int c = 0; c < 9; ++c) sh.item[c][tid] = sum[c];
+                for (int q = 0; q < PER; ++q) part[q] = 0.0f;
+                for (uint32_t e = b; e < b + n; ++e) {
+#pragma unroll
+                    for (int q = 0; q < PER; ++q) part[q] += sh.item[min(w0 + q * WAVES, 8)][e];
+                }
+#pragma unroll
+                for (int q = 0; q < PER; ++q)
+                    if (w0 + q * WAVES < 9) sh.sum[w0 + q * WAVES][lane] = part[q];
+            }
             __syncthreads();
-            if (wv == 0) {
 #pragma unroll
-                for (int w = 1; w < L::WAVES; ++w)
-#pragma unroll
-                    for (int c = 0; c < 9; ++c) sum[c] += sh.item[c][w * kWave + lane];
-            }
+            for (int c = 0; c < 9; ++c) sum[c] = sh.sum[c][lane];
         }
         if (tid >= kmin && tid < ncand) {
             {   // every entry's pair slot is written, zero sums included
@@ -459,7 +565,7 @@ __device__ __forceinline__ void bwd_tile(const BwdArgs& a, uint32_t tile, BwdSha
     // their pair slots get zeros here, so that every pair of the frame is
     // written by its tile's workgroup and the gather needs no cleared buffer.
     const int nlist = (int)(rg.y - rg.x);
-    for (int e = hi0 + tid; e < nlist; e += L::NCELL) {
+    for (int e = hi0 + tid; e < nlist; e += Tm::THREADS) {
         const uint32_t gid = a.vals[rg.x + (uint32_t)e];
         const ushort4 r = a.rect[gid];
         const int64_t p = (int64_t)a.first[gid] + (int64_t)(ty - (int)r.y) * ((int)r.z - (int)r.x) + (tx - (int)r.x);
@@ -471,20 +577,20 @@ __device__ __forceinline__ void bwd_tile(const BwdArgs& a, uint32_t tile, BwdSha
     }
 }
 
-template <class L, bool STORED, int CAP>
-__global__ __launch_bounds__(L::NCELL) void k_render_bwd(BwdArgs a) {
-    __shared__ BwdShared<L, CAP> sh;
+template <class L, int LPC, bool STORED, int CAP>
+__global__ __launch_bounds__(L::NCELL * LPC) void k_render_bwd(BwdArgs a) {
+    __shared__ BwdShared<L, LPC, CAP> sh;
     uint32_t tile = blockIdx.x;
     if (a.torder) {
         if (a.torder_n && blockIdx.x >= *a.torder_n) return;
         tile = a.torder[blockIdx.x];
     }
-    bwd_tile<L, STORED, CAP>(a, tile, sh);
+    bwd_tile<L, LPC, STORED, CAP>(a, tile, sh);
 }
 
 template <class L, int CAP>
 __global__ __launch_bounds__(L::NCELL) void k_render_bwd_persistent(BwdArgs a) {
-    __shared__ BwdShared<L, CAP> sh;
+    __shared__ BwdShared<L, 1, CAP> sh;
     __shared__ uint32_t s_next;
     for (;;) {
         __syncthreads();
@@ -492,7 +598,7 @@ __global__ __launch_bounds__(L::NCELL) void k_render_bwd_persistent(BwdArgs a) {
         __syncthreads();
         const uint32_t q = s_next;
         if (q >= a.n_tiles) break;
-        bwd_tile<L, false, CAP>(a, a.order ? a.order[q] : q, sh);
+        bwd_tile<L, 1, false, CAP>(a, a.order ? a.order[q] : q, sh);
     }
 }
 
@@ -531,18 +637,17 @@ __global__ __launch_bounds__(256) void k_pair_gather(int64_t nslots, const uint3
 template <int TW, int TH>
 void launch_t(const BwdArgs& a, int persistent_grid, int cap, hipStream_t st) {
     using L = typename CellsFor<TW, TH>::L;
-    using F = typename FineCellsFor<TW, TH>::L;
     const dim3 block(L::NCELL);
-    if constexpr (F::NCELL > L::NCELL) {
-        if (!a.state && (int64_t)a.n_tiles * L::WAVES <= kFineBwdWaves) {
+    if constexpr (L::NP > 1) {
+        constexpr int LPC = L::NP < kTeamLanes ? L::NP : kTeamLanes;
+        if (!a.state && (int64_t)a.n_tiles * L::WAVES <= kTeamMaxWaves) {
             // whatever launch form was asked for: so few tiles need no queue
             BwdArgs f = a;
-            f.masks = nullptr;
             if (persistent_grid > 0) {
                 f.torder = a.order;   // every tile
                 f.torder_n = nullptr;
             }
-            hipLaunchKernelGGL((k_render_bwd<F, false, kFineCap>), dim3(a.n_tiles), dim3(F::NCELL), 0, st, f);
+            hipLaunchKernelGGL((k_render_bwd<L, LPC, false, kTeamCap>), dim3(a.n_tiles), dim3(L::NCELL * LPC), 0, st, f);
             return;
         }
     }
@@ -552,14 +657,14 @@ void launch_t(const BwdArgs& a, int persistent_grid, int cap, hipStream_t st) {
         // walk and nowhere else
         BwdArgs f = a;
         f.masks = nullptr;
-        hipLaunchKernelGGL((k_render_bwd<L, true, kItemCap>), dim3(a.n_tiles), block, 0, st, f);
+        hipLaunchKernelGGL((k_render_bwd<L, 1, true, kItemCap>), dim3(a.n_tiles), block, 0, st, f);
     } else if (persistent_grid > 0 && cap == kItemCapSmall && kItemCapSmall >= L::NCELL) {
         hipLaunchKernelGGL((k_render_bwd_persistent<L, (kItemCapSmall >= L::NCELL ? kItemCapSmall : kItemCap)>),
                            dim3(persistent_grid), block, 0, st, a);
     } else if (persistent_grid > 0) {
         hipLaunchKernelGGL((k_render_bwd_persistent<L, kItemCap>), dim3(persistent_grid), block, 0, st, a);
     } else {
-        hipLaunchKernelGGL((k_render_bwd<L, false, kItemCap>), dim3(a.n_tiles), block, 0, st, a);
+        hipLaunchKernelGGL((k_render_bwd<L, 1, false, kItemCap>), dim3(a.n_tiles), block, 0, st, a);
     }
 }
 
