@@ -19,7 +19,9 @@
 // D-SSIM term at pixel q is (G*dm)(q) + 2 x(q) (G*dE)(q) + y(q) (G*dX)(q),
 // the maps dm, dE, dX being zero outside the image.
 //
-// Two kernels compute the same bits (the same sums in the same order):
+// Two kernels compute the same gradient bits (the same sums in the same
+// order); the loss value they add in their own order each, no lane more than
+// a few pixels in FP32:
 //
 // k_loss_tile, for small images.  One workgroup computes one 32 x 32 output
 // tile of one channel entirely in LDS: the input with a 10-pixel halo, the
@@ -134,7 +136,8 @@ struct LossArgs {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ float wave_sum(float v) {
+template <class T>
+__device__ __forceinline__ T wave_sum(T v) {
     for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
     return v;
 }
@@ -487,7 +490,7 @@ struct LossLds {
     // the step in which a value that a zero weight would not cancel was
     // staged; looked at one step later, so that every thread sees the same
     int big;
-    float red[2][kColWaves];
+    double red[2][kColWaves];
 };
 
 // One workgroup's segment; false (for every thread alike) when a big value
@@ -527,7 +530,7 @@ __device__ __forceinline__ bool segment(const LossArgs& a, LossLds& L, int lb, c
 #pragma unroll
             for (int q = 0; q < 5; ++q) acc[q][k] = f4{0.f, 0.f, 0.f, 0.f};
         const float gs = a.gs;
-        float ssum = 0.f;
+        double ssum = 0.0;   // a lane's sum runs down the whole segment: FP64 above a group's four rows
         float nx[kG], ny[kG];   // the rows staged next
         auto load = [&](int n) {
 #pragma unroll
@@ -567,7 +570,7 @@ __device__ __forceinline__ bool segment(const LossArgs& a, LossLds& L, int lb, c
                 add_rows<PLAIN, 5>(h, kw, a.win, acc, m);
                 if (n >= 3) {
                     float* dst = L.p[n & 1] + col;
-                    float worst = 0.f;
+                    float worst = 0.f, group = 0.f;
 #pragma unroll
                     for (int i = 0; i < kG; ++i) {
                         const int py = y0 - kR + kG * (n - 3) + i;
@@ -578,7 +581,7 @@ __device__ __forceinline__ bool segment(const LossArgs& a, LossLds& L, int lb, c
                         const float inv = __builtin_amdgcn_rcpf(b1 * b2);
                         const float S = a1 * a2 * inv;
                         const bool in = ss_col && py >= 0 && py < H;
-                        if (in && sum_col && py >= y0 && py < y1) ssum += S;
+                        if (in && sum_col && py >= y0 && py < y1) group += S;
                         const float p0 = in ? gs * 2.f * inv * (my * (a2 - a1) - mx * S * (b2 - b1)) : 0.f;
                         const float p1 = in ? -gs * S * b1 * inv : 0.f;
                         const float p2 = in ? gs * 2.f * a1 * inv : 0.f;
@@ -587,6 +590,7 @@ __device__ __forceinline__ bool segment(const LossArgs& a, LossLds& L, int lb, c
                         dst[(kG + i) * kStride] = p1;
                         dst[(2 * kG + i) * kStride] = p2;
                     }
+                    ssum += (double)group;
                     if (!PLAIN && !(worst < kBig)) L.big = n;
                 }
             }
@@ -609,7 +613,7 @@ __device__ __forceinline__ bool segment(const LossArgs& a, LossLds& L, int lb, c
         float* __restrict__ dx = a.dx + plane;
         float* __restrict__ dxa = eq3 ? a.dxa + plane : nullptr;
         const float g1 = a.g1;
-        float l1sum = 0.f;
+        double l1sum = 0.0;
         // the partials staged in step n; output rows group n - 6
         auto take = [&](int n) {
             float xo[kG], yo[kG], ao[kG];   // the inputs at the output rows
@@ -626,6 +630,7 @@ __device__ __forceinline__ bool segment(const LossArgs& a, LossLds& L, int lb, c
             row_sums<PLAIN, false, 3>(L.p[n & 1] + cw * kWave, lane, kw, a.win, h);
             add_rows<PLAIN, 3>(h, kw, a.win, acc, d);
             if (n < 6) return;
+            float group = 0.f;
 #pragma unroll
             for (int i = 0; i < kG; ++i) {
                 const int py = y0 + kG * (n - 6) + i;
@@ -634,11 +639,12 @@ __device__ __forceinline__ bool segment(const LossArgs& a, LossLds& L, int lb, c
                 const float ds = d[0][i] + 2.f * xo[i] * d[1][i] + yo[i] * d[2][i];
                 if (out_col && py < y1) {
                     const int64_t q = (int64_t)py * W + oxc;
-                    l1sum += fabsf(df);
+                    group += fabsf(df);
                     dx[q] = eq3 ? ds : ds + d1;
                     if (eq3) dxa[q] = d1;
                 }
             }
+            l1sum += (double)group;
         };
         __syncthreads();
         for (int n = 0; n < steps; ++n) {
@@ -655,12 +661,12 @@ __device__ __forceinline__ bool segment(const LossArgs& a, LossLds& L, int lb, c
     // ---- per-workgroup partial sums
     __syncthreads();
     if (tid == 0) {
-        float s = 0.f, l = 0.f;
+        double s = 0.0, l = 0.0;
         for (int k = 0; k < kColWaves; ++k) {
             s += L.red[0][k];
             l += L.red[1][k];
         }
-        a.partial[lb] = make_float2(s, l);
+        a.partial[lb] = make_float2((float)s, (float)l);
     }
     return true;
 }

@@ -197,3 +197,17 @@ def test_values_that_are_not_finite_reach_their_windows_only(C, y, x, value):
     assert np.isnan(d).sum() == np.isnan(rd).sum()
     ok = ~np.isnan(rd)
     grad_close("d_image", d[lo:hi][ok], rd[ok])
+
+
+@pytest.mark.parametrize("C,H,W", [(3, 2160, 3840), (600, 130, 44)])
+@pytest.mark.parametrize("x,y", [(0.7, 0.4), (0.3, 0.17), (0.8, 0.13)])
+def test_mean_of_a_uniform_difference_over_long_segments(C, H, W, x, y):
+    """Segments of 216 and 132 rows whose every L1 term is the same number: a
+    lane that adds them one by one in FP32 drifts by some 1e-6 of the sum.
+    At most four terms are added in FP32, then FP64 sums are rounded once a
+    segment and once at the end: 2 + 1 + 1 roundings of 2^-24."""
+    _case(f"uniform |{x} - {y}| C={C} H={H} W={W}")
+    r, t = (torch.full((C, H, W), v, dtype=torch.float32, device="cuda") for v in (x, y))
+    out, _, _ = gl.image_loss(r, t, 0.2)
+    want = float(np.float32(x) - np.float32(y))
+    assert abs(float(out[1]) / want - 1.0) <= 4 * 2.0 ** -24
