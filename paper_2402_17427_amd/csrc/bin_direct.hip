@@ -274,7 +274,11 @@ __global__ __launch_bounds__(kDThreads) void k_dscan(DTab views, int strips, int
 }
 
 // The rectangles of more than kDLarge tiles among a wave's, one after another
-// with a lane a tile: f(owner's lane, tile column, tile row).  A lane that
+// with a lane a tile: f(pair, tile column, tile row), the pair being the
+// owner's depth z (high word) and slot i.  They are read from the owner's
+// lane here, where the whole wave is active: in the loop over the tiles the
+// owner may not be, and a value computed or reloaded there would be stale in
+// its registers.  A lane that
 // walks its own rectangle makes the wave wait an LDS round trip a tile, for
 // its largest rectangle four times a round.  With the loads above, 4M
 // Gaussians on 32400 tiles: 74 -> 53 us; 1M on 8160: 21 -> 18; limits of 4,
@@ -282,7 +286,7 @@ __global__ __launch_bounds__(kDThreads) void k_dscan(DTab views, int strips, int
 // side, a step for the largest of the wave: 130.  Counting needs no answer
 // from the LDS and gained nothing from it (38.8 -> 41 us for eight views).
 template <class F>
-__device__ __forceinline__ void each_large_rect(ushort4 r, uint32_t area, F f) {
+__device__ __forceinline__ void each_large_rect(ushort4 r, uint32_t area, float z, uint32_t i, F f) {
     const int lane = threadIdx.x & (kWave - 1);
     uint64_t todo = __ballot(area > kDLarge);
     while (todo) {
@@ -291,9 +295,11 @@ __device__ __forceinline__ void each_large_rect(ushort4 r, uint32_t area, F f) {
         const int x0 = __builtin_amdgcn_readlane(r.x, l), y0 = __builtin_amdgcn_readlane(r.y, l);
         const int w = __builtin_amdgcn_readlane(r.z, l) - x0;
         const int n = __builtin_amdgcn_readlane((int)area, l);
+        const uint64_t pair = (uint64_t)(uint32_t)__builtin_amdgcn_readlane(__float_as_int(z), l) << 32 |
+                              (uint32_t)__builtin_amdgcn_readlane((int)i, l);
         for (int p = lane; p < n; p += kWave) {
             const int y = p / w;
-            f(l, x0 + p - y * w, y0 + y);
+            f(pair, x0 + p - y * w, y0 + y);
         }
     }
 }
@@ -440,10 +446,9 @@ __global__ __launch_bounds__(kDThreads) void k_dscatter(DTab views, const ushort
                         pairs[pos] = hi | (uint32_t)(i0 + k);
                     }
             }
-            each_large_rect(r[k], a[k], [&](int l, int tx, int ty) {
+            each_large_rect(r[k], a[k], z[k], (uint32_t)(i0 + k), [&](uint64_t pair, int tx, int ty) {
                 const uint32_t pos = atomicAdd(&s_cur[ty * ntx + tx], 1u);
-                pairs[pos] = (uint64_t)(uint32_t)__builtin_amdgcn_readlane(__float_as_int(z[k]), l) << 32 |
-                             (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(i0 + k), l);
+                pairs[pos] = pair;
             });
         }
     }
@@ -981,7 +986,7 @@ void launch_bin_direct_sort(uint32_t n_tiles, int64_t capacity, uint64_t* keys, 
     }
     const unsigned blocks = (unsigned)((n_tiles + kDSortWaves - 1) / kDSortWaves) +
                             (tile_order ? order_blocks(n_tiles) : 0u);
-    // long-run workgroups after the others: as many as there can be long
+    // long-run workgroups, ahead of the short runs: as many as there can be long
     // runs (one per kDSortCap + 1 pairs of capacity, at most one per tile),
     // so that they run side by side
     int64_t lg = capacity / (kDSortCap + 1);
