@@ -85,17 +85,18 @@ struct BwdArgs {
 // walk is shorter: a lane evaluates one pixel instead of four, and a wave
 // waits for the longest of 16 cells' lists instead of 64.  Measured, one lane
 // -> team: 2000 Gaussians at 128 x 128 (64 tiles of 16 x 16) 91 -> 56 us, 20k
-// at 400 x 400 49 -> 40, 200k at 800 x 800 (2500 tiles) 194 -> 158, at 600 x
-// 500 298 -> 237; 200k at 800 x 800 in tiles of 32 x 8 191 -> 160 (2500
-// waves), of 32 x 16 271 -> 224, of 32 x 32 375 -> 325; 200k at 672 x 480 in
-// tiles of 16 x 8 (2520 waves) 128 -> 127.  The team issues more instructions
-// in all, so it loses once the chip is full, from 2900 waves on with few
-// Gaussians and 4900 with many: 2478 waves 41 -> 40 (20k Gaussians), 95 -> 79
-// (100k), 254 -> 207 (400k) and 430 -> 350 (1M); 3381: 47 -> 49, 93 -> 91,
-// 215 -> 174 and 360 -> 319; 4368: 53 -> 59, 91 -> 102, 191 -> 176 and 307 ->
-// 330; 5185: 58 -> 68, 93 -> 112, 177 -> 186 and 294 -> 339.  The line is the
-// largest size at which it gained everywhere.  512 slots: 69 us for the box;
-// 2048: as 1024 there, 208 at 800 x 800.
+// at 400 x 400 50 -> 41, 200k at 800 x 800 (2500 tiles) 196 -> 159, at 600 x
+// 500 298 -> 236; 200k at 800 x 800 in tiles of 32 x 8 191 -> 160 (2500
+// waves), of 32 x 16 271 -> 224, of 32 x 32 369 -> 326; 200k at 672 x 480 in
+// tiles of 16 x 8 (2520 waves) 128 -> 126.  The team issues more instructions
+// in all, so it loses once the chip is full, from 2700 waves on with short
+// lists and 5000 with long ones: 2478 waves 42 -> 40 (20k Gaussians), 96 -> 79
+// (100k), 256 -> 207 (400k) and 430 -> 348 (1M); 2880: 41 -> 44, 94 -> 86,
+// 241 -> 195 and 398 -> 322; 3381: 43 -> 49, 93 -> 90, 215 -> 173 and 366 ->
+// 314; 4368: 51 -> 59, 92 -> 103, 193 -> 175 and 309 -> 325; 5185: 54 -> 68,
+// 93 -> 112, 177 -> 185 and 287 -> 334.  Below the line only nearly empty
+// images lose (20k Gaussians over 100 m, 2478 waves: 23 -> 27 us).  512 slots:
+// 69 us for the box; 2048: 56, and 208 at 800 x 800.
 constexpr int64_t kTeamMaxWaves = 2560;
 constexpr int kTeamLanes = 4;
 constexpr int kTeamCap = 1024;
@@ -134,6 +135,9 @@ __device__ __forceinline__ void share(const float (&own)[PPL], float (&all)[PPL 
     }
 }
 
+// (One wave a tile: 22800 bytes, seven workgroups a CU.  LDS is given out in
+// units of 1280 bytes: 241 more would make it six, 230 -> 254 us for 1M
+// Gaussians at 1920 x 1080.)
 template <class L, int LPC, int CAP>
 struct BwdShared {
     static constexpr int WAVES = Team<L, LPC>::WAVES;
@@ -146,7 +150,7 @@ struct BwdShared {
     uint32_t base[WAVES][kChunk];   // items per (wave, entry), then their first slot
     uint32_t total[kChunk];         // items per entry
     float item[9][CAP];             // the nine sums of each (cell, entry)
-    float sum[WAVES > 1 ? 9 : 1][kChunk];   // ... and of each entry
+    float sum[WAVES > 1 ? 9 : 1][WAVES > 1 ? kChunk : 1];   // ... and of each entry
     uint32_t max_last;
     int kmin;                       // the chunk: candidates kmin .. ncand - 1
 };
