@@ -419,9 +419,10 @@ gs_status gs_partition_views(const gs_camera *cams, int32_t n_views, const float
  * view_member [n_cells][n_views] are the host values of gs_partition_views.
  * point_member: device [n_cells][n_points], overwritten: 1 = in the
  * expanded rectangle, 2 = covered by a view of the cell, 0 = neither.
- * tests: device uint64 counter of the projections performed (work counter,
- * added to; a point decided with all its neighbours at once counts one), or
- * NULL.  ws: device scratch of gs_select_points_workspace()
+ * tests: device uint64 counter, added to, or NULL: one for every view that a
+ * point outside a cell's rectangle was projected into, and one for every such
+ * (point, cell) that was decided with all its neighbours at once, without a
+ * projection.  ws: device scratch of gs_select_points_workspace()
  * bytes (n_points < 2^32); the call uploads the camera and cell tables into
  * it and synchronises `stream` once before launching.  A view whose image
  * holds (or misses) the whole box around a ground square's points decides

@@ -259,8 +259,9 @@ void launch_adam_prepare(AdamSched* s, hipStream_t st);
 constexpr int kCamDoubles = 20;
 // member[c][i] = 1 when point i's ground position (x, z) lies in cell c's
 // closed expanded rectangle cells[c] = (x0, x1, z0, z1), else 2 when one of
-// the cell's views covers it, else 0.  tests (optional) accumulates the
-// projections performed (a point decided with its whole grid square: one).
+// the cell's views covers it, else 0.  tests (optional) accumulates one for
+// every projection and one for every (point, cell) decided with the point's
+// grid square instead: no measure of the arithmetic done.
 struct SelectArgs {
     const float* points;  // [3][ld]
     int64_t n, ld;

@@ -98,3 +98,14 @@ def test_cameras_packed_together_equal_cameras_packed_one_by_one(n):
             cams = [variant(c, (k + i) % 5 if mixed else k) for i, c in enumerate(base)]
             want = (N.gs_camera * n)(*[N.make_camera(c) for c in cams])
             assert bytes(N.make_cameras(cams)) == bytes(want)
+
+
+def test_selection_roofline_stands_on_the_bytes_of_its_inputs_and_outputs():
+    """Most points are decided with their ground square, without a
+    projection, so the work counter is no count of arithmetic: the bench
+    line's selection figure is the bytes of points in and members out."""
+    import inspect
+    import bench
+    assert bench.select_bytes(2_000_000, 8) == 2_000_000 * (3 * 4 + 8)
+    src = inspect.getsource(bench.bench_partition)
+    assert "select_bytes(" in src and "work_lane_ops" not in src
