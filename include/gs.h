@@ -518,7 +518,9 @@ typedef struct {
 
 typedef struct {
     int32_t tile_w, tile_h;     /* tile shape (0 = 16x16) */
-    int32_t persistent;         /* 1 = persistent blend grids with a longest-first tile queue */
+    int32_t persistent;         /* 1 = persistent blend grids with a longest-first tile queue (a blend of few
+                                 * tiles takes one workgroup per tile all the same, unless one of the three
+                                 * fields below is set) */
     int32_t use_graph;          /* 1 = capture the step as a hipGraph */
     int32_t autotune;           /* 1 = time the candidate shapes/forms at creation, keep the fastest */
     double capacity_headroom;   /* pair capacity = headroom x pairs needed at creation (<= 1: 1.25) */
@@ -531,7 +533,9 @@ typedef struct {
     int32_t grid_pct;           /* grid = this % of the workgroups that fit at once: 0 = 100, 1..100 */
 } gs_batch_config;              /* NULL = {16, 16, 1, 1, 0, 1.25, 0, NULL, 0, 0, 0} */
 typedef struct {
-    int32_t tile_w, tile_h, persistent, use_graph, grid_fwd, grid_bwd;
+    int32_t tile_w, tile_h, persistent, use_graph;
+    int32_t grid_fwd, grid_bwd;   /* workgroups of the persistent grids; with `persistent` asked for, 0 = that blend
+                                   * is of few tiles and takes one workgroup per tile (persistent = 0: both do) */
     uint32_t n_tiles;
     int64_t slots, pair_capacity;
     int32_t n_candidates;       /* autotune: candidates timed, in order */

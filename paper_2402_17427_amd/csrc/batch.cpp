@@ -92,7 +92,10 @@ struct gs_batch {
 
     // chosen configuration
     int tw = 16, th = 16, persistent = 1, use_graph = 1;
-    int grid_fwd = 0, grid_bwd = 0;
+    // the persistent form is as named (a candidate's, or with knobs of the
+    // caller's), else blends too small for it take one workgroup per tile
+    bool as_named = false;
+    int grid_fwd = 0, grid_bwd = 0;   // of the persistent grids; 0: that blend is too small
     int fwd_batch = 0, item_cap = 0, grid_pct = 100;   // persistent grids: LDS knobs (0 = default), grid share
     uint32_t n_tiles = 0;
     int64_t capacity = 0;
@@ -222,6 +225,10 @@ struct gs_batch {
             return check_hip("gs_batch: view table upload");
         grid_fwd = std::max(1, render_persistent_grid(w, h, false, fwd_batch) * grid_pct / 100);
         grid_bwd = std::max(1, render_persistent_grid(w, h, true, item_cap) * grid_pct / 100);
+        if (persistent && !as_named) {
+            if (render_fwd_small(w, h, n_tiles)) grid_fwd = 0;
+            if (render_bwd_small(w, h, n_tiles)) grid_bwd = 0;
+        }
         return GS_OK;
     }
 
@@ -446,6 +453,7 @@ gs_status gs_batch_create(const gs_gaussians* cells, const gs_camera* cams, cons
         if (cfg->grid_pct < 1 || cfg->grid_pct > 100) s = fail(GS_ERR_INVALID, "grid_pct %d not in 1..100", cfg->grid_pct);
         else b->grid_pct = cfg->grid_pct;
     }
+    b->as_named = autotune || (cfg && (cfg->fwd_batch || cfg->item_cap || cfg->grid_pct));
     if (!s && (!std::isfinite(b->lambda) || b->lambda < 0.f)) s = fail(GS_ERR_INVALID, "loss_lambda must be >= 0");
     const gs_batch_optim* opt = cfg ? cfg->optim : nullptr;
     if (!s && opt) s = check_batch_optim(opt, cells, grads, n_cells);
@@ -654,7 +662,7 @@ gs_status gs_batch_info(const gs_batch* b, gs_batch_stats* info) {
     std::memset(info, 0, sizeof *info);
     info->tile_w = b->tw;
     info->tile_h = b->th;
-    info->persistent = b->persistent;
+    info->persistent = b->persistent && (b->grid_fwd > 0 || b->grid_bwd > 0);
     info->use_graph = b->use_graph && b->exec != nullptr;
     info->grid_fwd = b->grid_fwd;
     info->grid_bwd = b->grid_bwd;

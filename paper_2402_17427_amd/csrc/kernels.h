@@ -132,7 +132,8 @@ void launch_bin_direct_sort(int64_t n, int64_t n_tiles, int64_t capacity, uint64
 // all views' tiles (global tile ids), status, the view table and the tile
 // shape.  With `queue` set (one device uint32, zeroed by the launcher) and
 // persistent_grid > 0 the launch is a persistent grid pulling tiles from
-// `order` (a permutation of the tiles, or NULL for 0, 1, ...).
+// `order` (a permutation of the tiles, or NULL for 0, 1, ...), whatever its
+// size; else launches of few tiles share each tile among more lanes.
 struct RenderArgs {
     const Rec* rec;
     const uint32_t* vals;
@@ -193,6 +194,10 @@ void launch_pair_gather(int64_t nslots, const uint32_t* first, const uint32_t* t
 // Workgroups of a persistent blend launch that fit on the device at once
 // (lds_knob: the fwd_batch or item_cap it will run with, 0 = default).
 int render_persistent_grid(int tw, int th, bool backward, int lds_knob = 0);
+// Whether one-workgroup-per-tile launches of so many tiles take the small
+// launches' layout: the form that is faster than a persistent grid there.
+bool render_fwd_small(int tw, int th, int64_t n_tiles);
+bool render_bwd_small(int tw, int th, int64_t n_tiles);
 int render_fwd_batch_default();
 int render_fwd_batch_small();
 int render_item_cap_default();

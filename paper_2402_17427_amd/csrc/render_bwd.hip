@@ -644,14 +644,8 @@ void launch_t(const BwdArgs& a, int persistent_grid, int cap, hipStream_t st) {
     const dim3 block(L::NCELL);
     if constexpr (L::NP > 1) {
         constexpr int LPC = L::NP < kTeamLanes ? L::NP : kTeamLanes;
-        if (!a.state && (int64_t)a.n_tiles * L::WAVES <= kTeamMaxWaves) {
-            // whatever launch form was asked for: so few tiles need no queue
-            BwdArgs f = a;
-            if (persistent_grid > 0) {
-                f.torder = a.order;   // every tile
-                f.torder_n = nullptr;
-            }
-            hipLaunchKernelGGL((k_render_bwd<L, LPC, false, kTeamCap>), dim3(a.n_tiles), dim3(L::NCELL * LPC), 0, st, f);
+        if (!a.state && persistent_grid <= 0 && (int64_t)a.n_tiles * L::WAVES <= kTeamMaxWaves) {
+            hipLaunchKernelGGL((k_render_bwd<L, LPC, false, kTeamCap>), dim3(a.n_tiles), dim3(L::NCELL * LPC), 0, st, a);
             return;
         }
     }
@@ -730,6 +724,16 @@ void launch_render_bwd(const RenderArgs& r, const float* final_T, const uint32_t
     else if (r.tw == 32 && r.th == 16) GS_BWD(32, 16);
     else if (r.tw == 32 && r.th == 32) GS_BWD(32, 32);
 #undef GS_BWD
+}
+
+bool render_bwd_small(int tw, int th, int64_t n_tiles) {
+    int waves = 0;   // a tile in the usual layout
+    if (tw == 16 && th == 16) waves = CellsFor<16, 16>::L::WAVES;
+    else if (tw == 16 && th == 8) waves = CellsFor<16, 8>::L::WAVES;
+    else if (tw == 32 && th == 8) waves = CellsFor<32, 8>::L::WAVES;
+    else if (tw == 32 && th == 16) waves = CellsFor<32, 16>::L::WAVES;
+    else if (tw == 32 && th == 32) waves = CellsFor<32, 32>::L::WAVES;
+    return waves > 0 && n_tiles * waves <= kTeamMaxWaves;
 }
 
 int render_item_cap_default() { return kItemCap; }

@@ -359,13 +359,9 @@ void launch_t(const FwdArgs& a, int persistent_grid, int batch, bool fine, hipSt
     using F = typename FineCellsFor<TW, TH>::L;
     const dim3 block(L::NCELL);
     if constexpr (F::NCELL > L::NCELL) {
-        if (!a.stats && !a.state && (fine || (int64_t)a.n_tiles * (TW * TH) <= kFineFwdPixels)) {
-            FwdArgs f = a;
-            if (persistent_grid > 0) {
-                f.torder = a.order;   // every tile
-                f.torder_n = nullptr;
-            }
-            hipLaunchKernelGGL((k_render_fwd<F, kPlain>), dim3(a.n_tiles), dim3(F::NCELL), 0, st, f);
+        if (!a.stats && !a.state && persistent_grid <= 0 &&
+            (fine || (int64_t)a.n_tiles * (TW * TH) <= kFineFwdPixels)) {
+            hipLaunchKernelGGL((k_render_fwd<F, kPlain>), dim3(a.n_tiles), dim3(F::NCELL), 0, st, a);
             return;
         }
     }
@@ -476,6 +472,10 @@ int render_persistent_grid_fwd(int tw, int th, int batch);
 
 int render_persistent_grid(int tw, int th, bool backward, int lds_knob) {
     return backward ? render_persistent_grid_bwd(tw, th, lds_knob) : render_persistent_grid_fwd(tw, th, lds_knob);
+}
+
+bool render_fwd_small(int tw, int th, int64_t n_tiles) {
+    return !(tw == 8 && th == 8) && n_tiles * (tw * th) <= kFineFwdPixels;   // 8 x 8 tiles have no finer cells
 }
 
 int render_fwd_batch_default() { return kBatch; }

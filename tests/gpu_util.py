@@ -20,6 +20,10 @@ Tolerances (written out here once, used by every GPU test):
 """
 from __future__ import annotations
 
+import math
+import os
+import re
+
 import numpy as np
 
 IMAGE_ATOL = 1e-4
@@ -107,3 +111,19 @@ def adam_close(pre_raw, pre_m, pre_v, grad_act, got, hyper, deg, step):
     assert np.all(np.abs(got["scale"] - act["scale"]) <= act["scale"] * (3e-7 + 1.0001 * tol_r[3:6]) + 1e-38), "scale"
     o = act["opacity"]
     assert np.all(np.abs(got["opacity"] - o) <= 3e-7 * o + o * (1 - o) * tol_r[10] + 1e-38), "opacity"
+
+
+def rule(source: str, name: str) -> int:
+    """A size limit of a launch rule, from the source that holds it: the
+    tests on both sides of the rule stay there when it moves."""
+    csrc = os.path.join(os.path.dirname(__file__), "..", "paper_2402_17427_amd", "csrc")
+    with open(os.path.join(csrc, source)) as f:
+        return int(re.search(rf"constexpr \w+ {name} = (\d+);", f.read()).group(1))
+
+
+# waves a tile in the blend backward's usual layout
+BWD_WAVES = {(16, 16): 1, (16, 8): 1, (32, 8): 1, (32, 16): 2, (32, 32): 4}
+
+
+def bwd_waves(tile, width: int, height: int) -> int:
+    return math.ceil(width / tile[0]) * math.ceil(height / tile[1]) * BWD_WAVES[tile]

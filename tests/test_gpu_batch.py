@@ -13,7 +13,7 @@ from gen import scenes
 from paper_2402_17427_amd import raster
 from paper_2402_17427_amd.batch import BatchStep
 
-from gpu_util import grad_close, image_close
+from gpu_util import bwd_waves, grad_close, image_close, rule
 
 pytestmark = pytest.mark.gpu
 
@@ -263,3 +263,83 @@ def test_batch_above_the_onesweep_grid_matches_plain_path():
         for k in PARAMS:
             grad_close(f"cell {c} {k}", got[k].cpu().numpy(), gr[k])
     b.close()
+
+
+def _run_batch(views, **kw):
+    dgs = [raster.DeviceGaussians.from_host(g) for g, _, _ in views]
+    b = BatchStep(dgs, [c for _, c, _ in views], [torch.as_tensor(t).cuda() for _, _, t in views], **kw)
+    scratch = torch.randn(1 << 18, device="cuda")
+    outs = []
+    for _ in range(3 if kw.get("use_graph", True) else 1):
+        b.step()
+        torch.cuda.synchronize()
+        scratch.mul_(1.0001).add_(1.0)      # eager work between replays
+        torch.cuda.synchronize()
+        assert b.status()[0] == 0
+        outs.append((b.images.cpu().numpy().copy(),
+                     [{k: v.cpu().numpy().copy() for k, v in b.cell_grads(c).items()} for c in range(len(views))]))
+    info, loss = b.info(), b.loss.cpu().numpy().copy()
+    b.close()
+    for images, grads in outs[1:]:
+        np.testing.assert_array_equal(images, outs[0][0], err_msg="replay")
+        for c, g in enumerate(grads):
+            for k in PARAMS:
+                np.testing.assert_array_equal(g[k], outs[0][1][c][k], err_msg=f"replay cell {c} {k}")
+    return *outs[0], loss, info
+
+
+def _same(a, b, what):
+    np.testing.assert_array_equal(a[0], b[0], err_msg=what)
+    for c, (x, y) in enumerate(zip(a[1], b[1])):
+        for k in PARAMS:
+            np.testing.assert_array_equal(x[k], y[k], err_msg=f"{what} cell {c} {k}")
+
+
+KNOBS = dict(fwd_batch=128, item_cap=256, grid_pct=60)
+
+
+@pytest.mark.parametrize("tile", [(16, 16), (32, 32)])
+def test_batch_above_the_small_launch_rules_runs_its_persistent_grids(tile):
+    """Views of more tiles than the small launches' rules take, where the
+    persistent grids, their LDS knobs and their graph replays are what runs:
+    every form gives the bits of the others, and the plain path's images,
+    losses and (within tolerance) gradients."""
+    _case(f"persistent grids tile={tile}")
+    views = []
+    for n, seed in ((6_000, 41), (9_000, 42)):
+        g, cam = scenes.small_city(n=n, seed=seed, width=1100, height=800, sh_degree=1)
+        views.append((g, cam, np.random.default_rng(seed).uniform(0, 1, (3, 800, 1100)).astype(np.float32)))
+    tiles = 2 * -(-1100 // tile[0]) * -(-800 // tile[1])
+    assert tiles * tile[0] * tile[1] > rule("render_fwd.hip", "kFineFwdPixels")
+    assert 2 * bwd_waves(tile, 1100, 800) > rule("render_bwd.hip", "kTeamMaxWaves")
+    a = _run_batch(views, tile=tile)
+    info = a[3]
+    assert info["persistent"] and info["grid_fwd"] > 0 and info["grid_bwd"] > 0
+    for kw in (KNOBS, dict(use_graph=False), dict(persistent=False), dict(persistent=False, use_graph=False)):
+        b = _run_batch(views, tile=tile, **kw)
+        assert b[3]["persistent"] == kw.get("persistent", True)
+        _same(a, b, str(kw))
+    off = 0
+    for c, (g, cam, tgt) in enumerate(views):
+        img, l1, gr = _plain(g, cam, tgt, tile)
+        np.testing.assert_array_equal(a[0][off:off + img.size].reshape(img.shape), img, err_msg=f"cell {c}")
+        off += img.size
+        assert abs(a[2][c] - l1) <= 1e-6 * max(l1, 1e-6) + 1e-7
+        for k in PARAMS:
+            grad_close(f"cell {c} {k}", a[1][c][k], gr[k])
+
+
+@pytest.mark.parametrize("tile", [(16, 16), (16, 8), (32, 16)])
+def test_batch_says_which_form_its_blends_run_in(tile):
+    """Blends too small for a persistent grid take one workgroup per tile and
+    the batch says so; with a knob of the caller's the grid runs as asked.
+    The forms agree bit for bit."""
+    _case(f"small batch tile={tile}")
+    views = _cells()
+    small = _run_batch(views, tile=tile)
+    assert not small[3]["persistent"] and small[3]["grid_fwd"] == small[3]["grid_bwd"] == 0
+    named = _run_batch(views, tile=tile, **KNOBS)
+    assert named[3]["persistent"] and named[3]["grid_fwd"] > 0 and named[3]["grid_bwd"] > 0
+    assert all(named[3][k] == v for k, v in KNOBS.items())
+    _same(small, named, "knobs")
+    _same(small, _run_batch(views, tile=tile, persistent=False), "plain")
