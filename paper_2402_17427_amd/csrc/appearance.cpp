@@ -105,7 +105,8 @@ void make_plan(int W, int H, int m, Plan* p) {
     p->gA = take(gmax);
     p->gB = take(gmax);
     p->part = take(pmax);
-    p->tmp = take(16 * (int64_t)H * (p->w * 16));   // x pass of the interpolation adjoint
+    // x pass of the interpolation adjoint
+    p->tmp = take(bilinear_adj_one_pass(H, W, p->h * 16) ? 0 : 16 * (int64_t)H * (p->w * 16));
     p->ty0 = take(H);
     p->ty1 = take(H);
     p->tfy = take(H);

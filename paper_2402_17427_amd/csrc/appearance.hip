@@ -1306,11 +1306,13 @@ void launch_bilinear(const float* in, int C, int h, int w, int H, int W, const B
                        W, t.y0, t.y1, t.fy, t.x0, t.x1, t.fx, out);
 }
 
+bool bilinear_adj_one_pass(int H, int W, int h) { return W <= kRowW && H >= h; }
+
 void launch_bilinear_adj(const float* g, int C, int H, int W, int h, int w, const BilinTab& t, float* tmp,
                          float* out, hipStream_t st) {
     hipLaunchKernelGGL(k_bilin_ranges, dim3(blocks_for(w)), dim3(kT), 0, st, w, W, t.x0, t.x1, t.xlo, t.xhi);
     hipLaunchKernelGGL(k_bilin_ranges, dim3(blocks_for(h)), dim3(kT), 0, st, h, H, t.y0, t.y1, t.ylo, t.yhi);
-    if (W <= kRowW && H >= h) {
+    if (bilinear_adj_one_pass(H, W, h)) {
         // bands that fill the chip's three workgroups a CU once, but of four
         // rows at least (each starts with the rows above its own)
         const int band = std::max(4, (int)(((int64_t)C * h + 767) / 768));

@@ -341,7 +341,8 @@ struct BilinTab {
 void launch_bilin_table(int n_in, int n_out, int* i0, int* i1, float* f, hipStream_t st);
 void launch_bilinear(const float* in, int C, int h, int w, int H, int W, const BilinTab& t, float* out,
                      hipStream_t st);
-// tmp: C H w floats of scratch
+// tmp: C H w floats of scratch, unless one pass does
+bool bilinear_adj_one_pass(int H, int W, int h);
 void launch_bilinear_adj(const float* g, int C, int H, int W, int h, int w, const BilinTab& t, float* tmp,
                          float* out, hipStream_t st);
 void launch_mul_bwd(const float* d_adj, const float* img, const float* M, int64_t n, float* dM, float* d_img,

@@ -220,3 +220,18 @@ def test_adam_step_validation_without_a_device():
     st.grad_accum = None
     assert step(cfg()) == N.GS_ERR_INVALID
     assert b"statistics" in lib.gs_last_error()
+
+
+@pytest.mark.parametrize("H", [33, 500])
+def test_appearance_workspace_holds_the_adjoint_map_only_where_two_passes_need_it(H):
+    """Up to 2048 columns (and no lower than its half-resolution map) the
+    interpolation adjoint is one pass without an intermediate map; a column
+    more and the workspace grows by that map, [16][H][w] floats, and by
+    little else."""
+    def query(W):
+        b = C.c_size_t()
+        assert N.lib().gs_appearance_workspace(W, H, 64, C.byref(b)) == N.GS_OK
+        return b.value
+    tmp = 16 * H * (2049 + 31) // 32 * 16 * 4
+    assert query(2049) - query(2048) >= tmp
+    assert query(2048) - query(2047) < tmp // 4
