@@ -243,11 +243,14 @@ __device__ __forceinline__ void project_slot(const Job& J, const Cam& cam, int64
     uint32_t count = 0;
 
     Geo g;
-    if (fin && (double)o >= 1.0 / 255.0 && geometry_view(cam, mu, g)) {
-        z = (float)g.t[2];
+    if (fin && geometry_view(cam, mu, g)) {
+        // every such Gaussian has its depth, seen or not, but those without a
+        // rotation (and below, where its SH planes are read, one with a
+        // non-finite coefficient)
+        z = q[0] * q[0] + q[1] * q[1] + q[2] * q[2] + q[3] * q[3] > 0.0 ? (float)g.t[2] : 0.f;
         out.u = (double)cam.fx * g.t[0] / g.t[2] + (double)cam.cx;
         out.v = (double)cam.fy * g.t[1] / g.t[2] + (double)cam.cy;
-        const bool seen = !off_screen(cam, s, o, out.u, out.v, g) && geometry_cov(s, q, g);
+        const bool seen = (double)o >= 1.0 / 255.0 && !off_screen(cam, s, o, out.u, out.v, g) && geometry_cov(s, q, g);
         const double det = seen ? g.a * g.c - g.b * g.b : 0.0;
         if (det > 0.0) {
             const double idet = 1.0 / det;
@@ -294,7 +297,9 @@ __device__ __forceinline__ void project_slot(const Job& J, const Cam& cam, int64
             y0 = fmax(y0, 0.0);
             x1 = fmin(x1, (double)(cam.W - 1));
             y1 = fmin(y1, (double)(cam.H - 1));
-            if (fin_sh && x0 <= x1 && y0 <= y1) {
+            if (!fin_sh) {   // as for any other non-finite input
+                z = 0.f;
+            } else if (x0 <= x1 && y0 <= y1) {
                 const int tx0 = (int)x0 / tw, tx1 = (int)x1 / tw + 1;
                 const int ty0 = (int)y0 / th, ty1 = (int)y1 / th + 1;
                 rc = make_ushort4((unsigned short)tx0, (unsigned short)ty0, (unsigned short)tx1, (unsigned short)ty1);
