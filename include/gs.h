@@ -112,7 +112,9 @@ typedef struct {
  *         power = -0.5 (A dx^2 + C dy^2) - B dx dy); float opacity;
  *         float r, g, b (colour); float thr = -log2(255 opacity), the
  *         base-2 exponent above which alpha >= 1/255 }.
- *   depth n floats: camera-space z (the sort key).
+ *   depth n floats: camera-space z (the sort key); 0 for a Gaussian behind the
+ *   near plane, without a rotation or with a non-finite input (of the SH
+ *   planes only where they are read: not for Gaussians off the image).
  *   rect  n x 4 uint16, 8-byte aligned: tile rectangle x0, y0, x1, y1
  *         (x1, y1 exclusive).
  *   tiles_touched n uint32: (x1 - x0) (y1 - y0), 0 for culled Gaussians.

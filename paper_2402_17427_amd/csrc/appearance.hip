@@ -1201,7 +1201,7 @@ void launch_down_adjoint(const float* g, int H, int W, int h, int w, float* d_im
 }
 
 int conv_splits(int Cin, int Cout, int H, int W) {
-    if (Cout <= 4) return 1;   // the VALU kernel
+    if (Cout <= 4) return 1;   // k_conv_few takes all channels
     // the low-resolution layers give too few workgroups to fill 256 CUs:
     // split their input channels until the grid has about 2048
     const int64_t wgs = (int64_t)((W + kTile - 1) / kTile) * ((H + kTile - 1) / kTile) * ((Cout + 15) / 16);

@@ -349,8 +349,9 @@ __global__ __launch_bounds__(L::NCELL) void k_render_fwd_persistent(FwdArgs a) {
 // 112 -> 100 with 1M but 29 -> 31 with 200k; 1700 x 1000 101 -> 103; 1920 x
 // 1080 100 -> 113 (32 x 16: 98 -> 87); 2560 x 1440 in 32 x 16 105 -> 116.
 // Launches that share the chip with others (`fine`) gain beyond it too: eight
-// requests on 100 cells 3300 -> 3000 us for the whole burst, five 2650 ->
-// 2230, one alone the same.
+// requests on 100 cells 3246 - 3333 -> 3002 - 3091 us for the whole burst,
+// five 2667 - 2727 -> 2314 - 2366 (the least and most of six runs each, in
+// turn), one alone the same.
 constexpr int64_t kFineFwdPixels = 1280000;
 
 template <int TW, int TH>
