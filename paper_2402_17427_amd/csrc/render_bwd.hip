@@ -96,7 +96,7 @@ struct BwdArgs {
 // 314; 4368: 51 -> 59, 92 -> 103, 193 -> 175 and 309 -> 325; 5185: 54 -> 68,
 // 93 -> 112, 177 -> 185 and 287 -> 334.  Below the line only nearly empty
 // images lose (20k Gaussians over 100 m, 2478 waves: 23 -> 27 us).  512 slots:
-// 69 us for the box; 2048: 56, and 208 at 800 x 800.
+// 69 us for the 64 tiles; 2048: 56, and 208 at 800 x 800.
 constexpr int64_t kTeamMaxWaves = 2560;
 constexpr int kTeamLanes = 4;
 constexpr int kTeamCap = 1024;
