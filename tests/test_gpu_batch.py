@@ -343,3 +343,20 @@ def test_batch_says_which_form_its_blends_run_in(tile):
     assert all(named[3][k] == v for k, v in KNOBS.items())
     _same(small, named, "knobs")
     _same(small, _run_batch(views, tile=tile, persistent=False), "plain")
+
+
+def test_batch_between_the_two_rules_mixes_the_forms():
+    """2816 tiles: few enough for the forward's rule, too many for the
+    backward's, so one blend takes one workgroup per tile and the other its
+    persistent grid, with the bits of either form alone."""
+    _case("mixed forms")
+    views = []
+    for n, seed in ((4_000, 51), (5_000, 52)):
+        g, cam = scenes.small_city(n=n, seed=seed, width=700, height=500, sh_degree=1)
+        views.append((g, cam, np.random.default_rng(seed).uniform(0, 1, (3, 500, 700)).astype(np.float32)))
+    assert 2 * 44 * 32 * 256 <= rule("render_fwd.hip", "kFineFwdPixels")
+    assert 2 * bwd_waves((16, 16), 700, 500) > rule("render_bwd.hip", "kTeamMaxWaves")
+    mixed = _run_batch(views)
+    assert mixed[3]["persistent"] and mixed[3]["grid_fwd"] == 0 and mixed[3]["grid_bwd"] > 0
+    _same(mixed, _run_batch(views, **KNOBS), "knobs")
+    _same(mixed, _run_batch(views, persistent=False), "plain")
